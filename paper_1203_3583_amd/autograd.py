@@ -20,7 +20,8 @@ def _torch():
 
 
 class _Propagate:
-    """Holder of the autograd.Function (built lazily so importing needs no torch)."""
+    """Holder of the autograd.Function (built lazily so importing needs no torch).  known:
+    u2, where the caller has it already."""
 
     fn = None
 
@@ -31,16 +32,16 @@ class _Propagate:
 
             class Propagate(torch.autograd.Function):
                 @staticmethod
-                def forward(ctx, u1, plan):
+                def forward(ctx, u1, plan, known):
                     ctx.plan = plan
-                    return plan.forward(u1.contiguous())
+                    return plan.forward(u1.contiguous()) if known is None else known.clone()
 
                 @staticmethod
                 def backward(ctx, grad_u2):
                     g = grad_u2
                     if g.dtype != torch.complex64:
                         g = g.to(torch.complex64)
-                    return ctx.plan.adjoint(g.contiguous()), None
+                    return ctx.plan.adjoint(g.contiguous()), None, None
 
             cls.fn = Propagate
         return cls.fn
@@ -48,7 +49,7 @@ class _Propagate:
 
 def propagate(plan, u1):
     """u2 = A u1 (complex64 [my, mx]) with autograd support through the adjoint."""
-    return _Propagate.get().apply(u1, plan)
+    return _Propagate.get().apply(u1, plan, None)
 
 
 class _IntensityLoss:
@@ -63,6 +64,9 @@ class _IntensityLoss:
             from . import asf as _asf
 
             class IntensityLoss(torch.autograd.Function):
+                # The field u1 is an output beside the loss: saved as one, it links a graph of
+                # the gradient to theta as it was at the forward, and nothing of the caller's
+                # (theta, amp, target may change in place) is read again.
                 @staticmethod
                 def forward(ctx, theta, plan, amp, target):
                     L = _asf.lib()
@@ -79,30 +83,45 @@ class _IntensityLoss:
                     _asf._check(L.asf_intensity_loss(m, u2.data_ptr(), target.data_ptr(),
                                                      int(target.dtype == torch.float64), diff, diff + 8 * m,
                                                      loss.data_ptr(), s))
+                    ctx.set_materialize_grads(False)
                     ctx.save_for_backward(u1, u2, buf)
-                    ctx.plan, ctx.args = plan, (theta, amp, target)
-                    return loss
+                    ctx.plan, ctx.theta = plan, (theta.shape, theta.dtype)
+                    return loss, u1
 
                 @staticmethod
-                def backward(ctx, grad):
+                def backward(ctx, grad, g1):
+                    """grad: of the loss, g1: of u1 (from a graph of the gradient); None: none."""
                     plan = ctx.plan
-                    theta, amp, target = ctx.args
-                    if torch.is_grad_enabled():   # create_graph: the composite's graph
-                        loss = _intensity_loss_composite(plan, theta, amp, target)
-                        return torch.autograd.grad(loss, theta, grad, create_graph=True)[0], None, None, None
-                    L = _asf.lib()
                     u1, u2, buf = ctx.saved_tensors
-                    dev, m = plan.device, plan.mx * plan.my
+                    m = plan.mx * plan.my
+                    shape, dtype = ctx.theta
+                    if torch.is_grad_enabled():   # create_graph: the same in differentiable operations
+                        if grad is not None:
+                            u = _Propagate.get().apply(u1, plan, u2)
+                            inten = u.real.double() ** 2 + u.imag.double() ** 2
+                            # the value saved, the derivative of the intensity
+                            d = buf[:m].view(plan.my, plan.mx) + (inten - inten.detach())
+                            part = torch.autograd.grad((d ** 2).sum() / buf[m], u1, grad, create_graph=True)[0]
+                            g1 = part if g1 is None else g1 + part
+                        out = None if g1 is None else (g1.conj() * (1j * u1)).real.to(dtype).reshape(shape)
+                        return out, None, None, None
+                    L = _asf.lib()
+                    dev = plan.device
                     s = _asf._stream_ptr(torch, dev, None)
-                    grad = grad.to(torch.float64).contiguous()
-                    g2 = torch.empty((plan.my, plan.mx), dtype=torch.complex64, device=dev)
-                    diff = buf.data_ptr()
-                    _asf._check(L.asf_intensity_loss_backward(m, u2.data_ptr(), diff, diff + 8 * m, grad.data_ptr(),
-                                                              g2.data_ptr(), s))
-                    g1 = plan.adjoint(g2)
-                    out = torch.empty_like(theta)
+                    if grad is not None:
+                        grad = grad.to(torch.float64).contiguous()
+                        g2 = torch.empty((plan.my, plan.mx), dtype=torch.complex64, device=dev)
+                        diff = buf.data_ptr()
+                        _asf._check(L.asf_intensity_loss_backward(m, u2.data_ptr(), diff, diff + 8 * m,
+                                                                  grad.data_ptr(), g2.data_ptr(), s))
+                        part = plan.adjoint(g2)
+                        g1 = part if g1 is None else g1 + part
+                    if g1 is None:
+                        return None, None, None, None
+                    g1 = g1.resolve_conj().contiguous()
+                    out = torch.empty(shape, dtype=dtype, device=dev)
                     _asf._check(L.asf_phase_backward(plan.n, u1.data_ptr(), g1.data_ptr(), out.data_ptr(),
-                                                     int(theta.dtype == torch.float64), s))
+                                                     int(dtype == torch.float64), s))
                     return out, None, None, None
 
             cls.fn = IntensityLoss
@@ -147,7 +166,7 @@ def intensity_loss(plan, theta, amp, target):
     target: real [my, mx] tensor in the units of |u2|^2 (see ``energy_matched``).
     """
     if _fused_loss_takes(plan, theta, amp, target):
-        return _IntensityLoss.get().apply(theta, plan, amp, target)
+        return _IntensityLoss.get().apply(theta, plan, amp, target)[0]
     return _intensity_loss_composite(plan, theta, amp, target)
 
 
