@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(NT) fft_pass1_kernel(const float2 *__restrict_
     using S = Shape<LOGL, BATCH, NT>;
     static_assert(MP % BATCH == 0, "mid panels hold whole column batches");
     extern __shared__ float2 lds[];
-    __shared__ float scratch[NT / 64];
+    __shared__ float scratch[NT / 64 * BATCH];
     __shared__ uint8_t lrow[kMaxTileRows];
     int pc = blockIdx.x;
     if (MP > BATCH && xcd_pair) {
@@ -200,7 +200,7 @@ __global__ void __launch_bounds__(NT) fft_pass2_kernel(const float2 *__restrict_
                                                        LiveTiles lt) {
     using S = Shape<LOGL, BATCH, NT>;
     extern __shared__ float2 lds[];
-    __shared__ float scratch[NT / 64];
+    __shared__ float scratch[NT / 64 * BATCH];
     __shared__ uint8_t lcol[kMaxTileCols];
     // workgroups are dealt to the 8 XCDs round-robin: give the xcd_group
     // workgroups whose rows share lines of mid consecutive slots on one XCD
@@ -278,7 +278,7 @@ __global__ void __launch_bounds__(NT) fft_adj_rows_kernel(const float2 *__restri
                                                           const float2 *__restrict__ dy, LiveTiles lt) {
     using S = Shape<LOGL, BATCH, NT>;
     extern __shared__ float2 lds[];
-    __shared__ float scratch[NT / 64];
+    __shared__ float scratch[NT / 64 * BATCH];
     __shared__ uint8_t lcol[kMaxTileCols];
     const int row0 = blockIdx.x * BATCH;
     const bool sparse = live_cols(lt, lcol);
@@ -333,7 +333,7 @@ __global__ void __launch_bounds__(NT) fft_adj_cols_kernel(const float2 *__restri
     using S = Shape<LOGL, BATCH, NT>;
     static_assert(FP == BATCH || FP == 1, "narrower fine-grid panels are single columns");
     extern __shared__ float2 lds[];
-    __shared__ float scratch[NT / 64];
+    __shared__ float scratch[NT / 64 * BATCH];
     __shared__ uint8_t lrow[kMaxTileRows];
     int pc = blockIdx.x;
     if (xcd_group > 1) {

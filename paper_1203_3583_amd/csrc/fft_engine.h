@@ -18,11 +18,12 @@
 //   split FP16 (matrix cores): the 16-point DFT as one small GEMM
 //     [Re Y; Im Y] (32 x 16) = W16 (32 x 32 real form of the DFT matrix) x [Re X; Im X] (32 x 16)
 //     with FP16 hi+lo split products (v_mfma_f32_16x16x32_f16: W_hi X_hi +
-//     W_hi X_lo + W_lo X_hi, FP32 accumulation).  The workgroup scales its data
-//     once, at load, by a power of two that brings the largest |Re|, |Im| to at
-//     most 1: FP16 carries its own exponent, so the scale only guards the
-//     range, and a transform of length L grows values by at most L <= 16384 <
-//     65504.
+//     W_hi X_lo + W_lo X_hi, FP32 accumulation).  Each transform is scaled once, at
+//     load, by a power of two that brings its largest |Re|, |Im| to at most 1: a
+//     transform of length L grows values by at most L <= 16384 < 65504, and values
+//     below 2^-3 of the largest, whose low halves are subnormal, keep 2^-25 of it.
+//     (With one scale for the workgroup's transforms a row 2^14 times dimmer than its
+//     neighbour was 1e-3 to 3e-3 off, with its own 2e-7; both take the same time.)
 // On gfx950 the FP32 matrix rate equals the FP32 vector rate, and a dense
 // 16-point DFT costs about six times the operations of the 4 x 4 network, so
 // FP32 products stay on the vector ALU.
@@ -147,7 +148,7 @@ struct Dft16Split16 {
             im_lo[e] = (_Float16)(b - (float)bh);
         }
     }
-    // inputs already scaled into FP16 range by the workgroup's scale
+    // inputs already scaled into FP16 range
     __device__ __forceinline__ void run(float2 (&v)[4]) const {
         v8h bh, bl;
 #pragma unroll
@@ -320,13 +321,18 @@ __device__ __forceinline__ void stages_from(float2 *lds, const float4 *tw, const
     }
 }
 
-__device__ __forceinline__ float block_max(float v, float *scratch) {
+// The largest v over a workgroup's lanes of the same transform: lane l of a wave holds
+// elements of transform l mod B, first-stage inputs and last-stage outputs alike (every
+// instance index and offset is a multiple of B plus the lane).
+template <int B>
+__device__ __forceinline__ float transform_max(float v, float *scratch) {
+    static_assert(B <= 16, "16 lanes of a block");
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
+    for (int off = 32; off >= B; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
+    if ((threadIdx.x & 63) < B) scratch[(threadIdx.x >> 6) * B + (threadIdx.x & 63)] = v;
     __syncthreads();
     float s = 0.f;
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s = fmaxf(s, scratch[i]);
+    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s = fmaxf(s, scratch[i * B + (threadIdx.x & (B - 1))]);
     return s;
 }
 
@@ -353,8 +359,9 @@ struct First {
 };
 
 // The workgroup's transforms from their inputs, the outputs (PRUNE: the kept ones only)
-// through out.  With SPLIT the inputs are scaled by the power of two that brings the
-// workgroup's largest |Re|, |Im| to at most 1 (and the outputs scaled back).
+// through out.  With SPLIT each transform's inputs are scaled by the power of two that
+// brings its largest |Re|, |Im| to at most 1 (and the outputs scaled back); scratch: B
+// floats per wave.
 template <class S, bool SPLIT, bool PRUNE, class Out>
 __device__ __forceinline__ void transform_loaded(float2 *lds, const float2 *tw, const float2 *w16, float *scratch,
                                                  float2 (&x)[First<S>::N][First<S>::R], const Out &out) {
@@ -373,7 +380,7 @@ __device__ __forceinline__ void transform_loaded(float2 *lds, const float2 *tw, 
         for (int a = 0; a < F::N; ++a)
 #pragma unroll
             for (int r = 0; r < F::R; ++r) big = fmaxf(big, fmaxf(fabsf(x[a][r].x), fabsf(x[a][r].y)));
-        const int e = range_exponent(block_max(big, scratch));
+        const int e = range_exponent(transform_max<S::B>(big, scratch));
         const float inv = ldexpf(1.f, -e);
         unscale = ldexpf(1.f, e);
 #pragma unroll

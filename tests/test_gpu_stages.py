@@ -554,3 +554,58 @@ def test_adjoint_stages_match_host(fft, bar, which):
     e3 = rel_l2(g1, want_g1)
     print(f"adjoint {fft}: rows {e1:.2e}, columns {e2:.2e}, interpolation {e3:.2e}")
     assert e1 <= bar and e2 <= bar and e3 <= 2e-6
+
+
+def _row_spectrum(mx, my, weight):
+    """Points on columns of a flat surface at the sampling where the destination rows are
+    the exact DFT of a column's points, so that row iy of the destination has amplitude
+    weight[iy] (times a random phase)."""
+    rng = np.random.default_rng(mx)
+    lam, z0, p2, cols = 532e-9, 0.1, 8e-6, 64
+    x = rng.uniform(-6e-4, 6e-4, cols)
+    y = lam * z0 / (p2 * my) * (np.arange(my) - my // 2)
+    Y = p2 * (np.arange(my) - my // 2)
+    a = weight * np.exp(2j * np.pi * rng.uniform(0, 1, my))
+    fy = np.exp(2j * np.pi * np.outer(y, Y) / (lam * z0)) @ a * np.exp(-1j * np.pi * y * y / (lam * z0))
+    fx = rng.standard_normal(cols) + 1j * rng.standard_normal(cols)
+    u = (fy[:, None] * fx[None, :]).reshape(-1).astype(np.complex64)
+    n = u.size
+    return synth.Workload("rows", np.tile(x, my), np.repeat(y, cols), np.zeros(n), u, lam, z0, p2, p2, mx, my)
+
+
+@pytest.mark.parametrize("mx", [16, 32, 64, 128, 512, 1024, 2048, 4096])
+def test_split_rows_keep_their_own_scale(mx):
+    """Bright rows beside rows 2^14 times dimmer, in the split-FP16 row pass: each row is as
+    accurate relative to itself as alone, whichever rows share its workgroup.
+
+    The bar: at a row's own scale each of the (at most three) radix-16 stages loses 2^-22 of
+    the values (their hi + lo), of the DFT matrix, and the dropped lo x lo product, 2.1e-6
+    for three stages, and the FP32 arithmetic, twiddles and tables some 2^-24 each, 1e-6 in
+    all; half as much again for the low halves that are subnormal (2^-25 of the row's
+    largest, a few times its rms).  At the bright row's scale those halves alone are 2^-11
+    of a dim row."""
+    torch = torch_gpu()
+    my = 32
+    weight = np.where(np.arange(my) % 2 == 0, 1.0, 2.0 ** -14)
+    w = _row_spectrum(mx, my, weight)
+    plan, u = _plan(torch, w, "split_fp16")
+    u2 = plan.forward(u).cpu().numpy().astype(np.complex128)
+    info = plan.info()
+    cols = _live_columns(torch, plan, info)
+    nfx, nfy, P = info["nfx"], info["nfy"], info["mid_panel"]
+    raw = _view(torch, plan, info["off_mid"], 2 * my * nfx, torch.float32)
+    plan.close()
+    mid = np.ascontiguousarray(raw).view(np.complex64).astype(np.complex128)
+    mid = np.where(cols[None, :], mid.reshape(nfx // P, my, P).transpose(1, 0, 2).reshape(my, nfx), 0.0)
+    rows = np.linalg.norm(mid, axis=1)
+    assert (rows[0::2] > 2.0 ** 12 * rows[1::2]).all() and (rows[1::2] > 0.0).all()
+    k = 2.0 * np.pi / w.lam
+    m, n = np.arange(mx) - mx // 2, np.arange(my) - my // 2
+    X, Y = w.p2x * m, w.p2y * n
+    dx = np.exp(1j * k * X * X / (2.0 * w.z0)) / _psi_hat(np.abs(m), nfx, info["w"], info["beta"])
+    dy = np.exp(1j * k * Y * Y / (2.0 * w.z0)) / _psi_hat(np.abs(n), nfy, info["w"], info["beta"])
+    pre = np.exp(1j * k * w.z0) / (1j * w.lam * w.z0)
+    want = pre * np.fft.fft(mid, axis=1)[:, m % nfx] * dy[:, None] * dx[None, :]
+    err = np.linalg.norm(u2 - want, axis=1) / np.linalg.norm(want, axis=1)
+    print(f"rows of {nfx}: bright {err[0::2].max():.2e}, dim {err[1::2].max():.2e}")
+    assert err.max() <= 4.7e-6
