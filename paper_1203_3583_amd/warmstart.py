@@ -183,23 +183,31 @@ class WarmNet:
     def infer(self, x):
         """The output of ``forward`` without keeping activations: the decoder's
         concatenations are read in place by their convolutions.  The activations share one
-        allocation and the eighteen launches are issued with plain addresses (at 512^2 the
-        kernels take about as long as a call per layer through torch tensors did)."""
+        allocation (120 floats per pixel at base 32) and the eighteen launches are issued
+        with plain addresses (at 512^2 the kernels take about as long as a call per layer
+        through torch tensors did)."""
         torch, sh = self.torch, self.shapes
         B, H, W, C = x.shape
         assert C == sh[0][0] and x.is_contiguous()
         L, s = _lib(), torch.cuda.current_stream().cuda_stream
         conv, upcat, pool = L.asf_warm_conv3x3, L.asf_warm_conv3x3_upcat, L.asf_warm_pool2
+        # Two places per level, for the first and the second convolution's result, the
+        # encoder's and then the decoder's: the first is read by the second convolution only,
+        # the second (the skip tensor) last by the decoder's first.  The first also takes the
+        # pooled second, the next level's input.
         px = [B * (H >> k) * (W >> k) for k in range(4)]
-        level = (0, 0, 1, 1, 2, 2, 3, 3, 2, 2, 1, 1, 0, 0)   # of layers 0 .. 13
-        sizes = [px[level[i]] * sh[i][1] for i in range(14)] + [px[k] * sh[2 * k - 1][1] for k in (1, 2, 3)]
+        enc, dec = (0, 2, 4, 6), (12, 10, 8, 6)   # each level's first layer
+        first = [max(px[k] * sh[i][1] for i in (enc[k], dec[k])) for k in range(4)]
+        second = [max(px[k] * sh[i + 1][1] for i in (enc[k], dec[k])) for k in range(4)]
+        for k in range(3):
+            first[k] = max(first[k], px[k + 1] * sh[enc[k] + 1][1])
         starts, total = [], 0
-        for n in sizes:
+        for n in first + second:
             starts.append(total)
             total += (n + 63) & ~63
         buf = torch.empty(total, dtype=torch.float32, device=x.device)
-        base = buf.data_ptr()
-        at = [base + 4 * o for o in starts]   # a0 .. a13, then the pooled a1, a3, a5
+        at = [buf.data_ptr() + 4 * o for o in starts]
+        first, second = at[:4], at[4:]
         out = torch.empty((B, H, W, sh[14][1]), dtype=torch.float32, device=x.device)
         wb, b = [t.data_ptr() for t in self.wb], [t.data_ptr() for t in self.b]
 
@@ -208,27 +216,28 @@ class WarmNet:
             _ok(conv(src, wb[i], b[i], dst, B, H >> k, W >> k, ci, co, int(r), s), "conv3x3")
 
         src = x.data_ptr()
-        for k in range(4):
-            layer(2 * k, src, at[2 * k], k)
-            layer(2 * k + 1, at[2 * k], at[2 * k + 1], k)
+        for k, i in enumerate(enc):
+            layer(i, src, first[k], k)
+            layer(i + 1, first[k], second[k], k)
             if k < 3:
-                src = at[14 + k]
-                _ok(pool(at[2 * k + 1], src, B, H >> k, W >> k, sh[2 * k + 1][1], s), "pool2")
-        low, cl = at[7], sh[7][1]
-        for i, skip, k in ((8, 5, 2), (10, 3, 1), (12, 1, 0)):
+                src = first[k]
+                _ok(pool(second[k], src, B, H >> k, W >> k, sh[i + 1][1], s), "pool2")
+        low, cl = second[3], sh[7][1]
+        for k in (2, 1, 0):
+            i, skip = dec[k], second[k]
             ci, co, r = sh[i]
-            h, w, cs = H >> k, W >> k, sh[skip][1]
+            h, w, cs = H >> k, W >> k, sh[enc[k] + 1][1]
             assert cl + cs == ci
-            if upcat(low, cl, at[skip], cs, wb[i], b[i], at[i], B, h, w, co, int(r), s) != 0:
+            if upcat(low, cl, skip, cs, wb[i], b[i], first[k], B, h, w, co, int(r), s) != 0:
                 # layers too small for the tiled kernel are concatenated first
                 up = torch.empty(B * h * w * (cl + ci), dtype=torch.float32, device=x.device)
                 u, c = up.data_ptr(), up.data_ptr() + 4 * B * h * w * cl
                 _ok(L.asf_warm_up2(low, u, B, h // 2, w // 2, cl, s), "up2")
                 _ok(L.asf_warm_copy_channels(u, cl, 0, c, ci, 0, cl, B * h * w, s), "concat")
-                _ok(L.asf_warm_copy_channels(at[skip], cs, 0, c, ci, cl, cs, B * h * w, s), "concat")
-                layer(i, c, at[i], k)
-            layer(i + 1, at[i], at[i + 1], k)
-            low, cl = at[i + 1], sh[i + 1][1]
+                _ok(L.asf_warm_copy_channels(skip, cs, 0, c, ci, cl, cs, B * h * w, s), "concat")
+                layer(i, c, first[k], k)
+            layer(i + 1, first[k], second[k], k)
+            low, cl = second[k], sh[i + 1][1]
         layer(14, low, out.data_ptr(), 0)
         return out
 

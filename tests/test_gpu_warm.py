@@ -315,3 +315,26 @@ def test_conv3x3_masked_matches_relu_backward(B, H, W, cin, cout):
     assert L.asf_warm_conv3x3_masked(ws._ptr(x), ws._ptr(w), ws._ptr(act), ws._ptr(out), B, H, W, cin, cout, s) == 0
     assert L.asf_warm_conv3x3(ws._ptr(x), ws._ptr(w), None, ws._ptr(plain), B, H, W, cin, cout, 0, s) == 0
     assert torch.equal(out, torch.where(act > 0, plain, torch.zeros_like(plain)))
+
+
+@pytest.mark.parametrize("B,H,W", [(1, 256, 256), (2, 320, 264)])
+def test_infer_keeps_no_activations(B, H, W):
+    """Memory asked for during one inference: at most what the layers one after the other
+    hold at the last two convolutions if the first activation, every skip tensor and every
+    level's result stay (32 + 32 + 16 + 8 + 4 + 8 + 16 + 32 channels at full resolution) and
+    the output."""
+    torch = torch_gpu()
+    from paper_1203_3583_amd.warmstart import WarmNet
+
+    net = WarmNet(base=32, seed=3)
+    x = torch.rand((B, H, W, 16), device="cuda")
+    out = net.infer(x)
+    assert torch.equal(out, net.forward(x)[0])
+    del out
+    torch.cuda.synchronize()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_stats()["requested_bytes.all.current"]
+    out = net.infer(x)
+    peak = torch.cuda.memory_stats()["requested_bytes.all.peak"] - before
+    print(f"{B} x {H} x {W}: {peak / (4 * B * H * W):.1f} channels")
+    assert out.shape == (B, H, W, 32) and peak <= 4 * B * H * W * (148 + 32)
