@@ -19,6 +19,7 @@ from __future__ import annotations
 
 import ctypes
 import math
+from collections.abc import MutableMapping
 
 from . import asf as _asf
 
@@ -91,33 +92,57 @@ def layer_shapes(c=32, cin0=16, cout_head=32):
             (c, cout_head, False)]
 
 
-class _LayerInputs(dict):
+class _LayerInputs(MutableMapping, dict):
     """The layers' inputs by layer.  A decoder layer whose concatenation was read in place
-    has (upsampled half, skip) here, and its tensor is formed when asked for."""
+    has (upsampled half, skip) here, and its tensor is formed when asked for, in whichever
+    way a dictionary can be asked; copies are plain dictionaries of tensors.  (The mapping's
+    methods go through those below, where a dictionary's own would read past them.)"""
 
     def __init__(self, net, items):
-        super().__init__(items)
+        dict.__init__(self, items)
         self._net = net
 
     def parts(self, i):
         """Layer i's input: one tensor, or (low, skip)."""
-        return super().__getitem__(i)
+        return dict.__getitem__(self, i)
 
     def __getitem__(self, i):
-        v = super().__getitem__(i)
+        v = dict.__getitem__(self, i)
         if isinstance(v, tuple):
             v = self._net._cat(self._net._up(v[0]), v[1])
             self[i] = v
         return v
 
-    def get(self, i, default=None):
-        return self[i] if i in self else default
+    def __iter__(self):
+        return dict.__iter__(self)
 
-    def values(self):
-        return [self[i] for i in self]
+    __len__, __contains__, __reversed__ = dict.__len__, dict.__contains__, dict.__reversed__
+    __setitem__, __delitem__, clear = dict.__setitem__, dict.__delitem__, dict.clear
 
-    def items(self):
-        return [(i, self[i]) for i in self]
+    def popitem(self):
+        if not self:
+            raise KeyError("popitem(): dictionary is empty")
+        i = next(reversed(self))
+        return i, self.pop(i)
+
+    def copy(self):
+        return dict(self)
+
+    def __or__(self, other):
+        return dict(self) | other
+
+    def __ror__(self, other):
+        return other | dict(self)
+
+    def __ior__(self, other):
+        self.update(other)
+        return self
+
+    def __repr__(self):
+        return repr(dict(self))
+
+    def __reduce_ex__(self, protocol):
+        return dict, (dict(self),)
 
 
 class WarmNet:
