@@ -169,3 +169,27 @@ def test_gather_paths(n, m, batch, spread):
     plan.close()
     for b in sorted({0, batch // 2, batch - 1}):
         assert rel_l2(got[b], _oracle(x, d, us[b], lam, z0, 8e-6, m)) <= TOL
+
+
+@pytest.mark.parametrize("n,m,batch", [
+    (6000, 1024, 2049),   # a thread per cell
+    (7000, 256, 2049),    # shared runs
+    (5500, 512, 2050),
+])
+def test_two_fields_per_workgroup_too_large_for_lds(n, m, batch):
+    """Batches of 2048 fields and more, two to a workgroup, gathered from memory: the first
+    and the last fields (with an odd batch the last workgroup has one) and one in between
+    against the oracle, and the same as each alone."""
+    torch = torch_gpu()
+    import paper_1203_3583_amd as asf
+
+    x, d, _, lam, z0 = _random_case(n, 0, 21, spread=2e-3)
+    plan = asf.LinePlan(torch.from_numpy(x).cuda(), torch.from_numpy(d).cuda(), lam, z0, 8e-6, m, tol=1e-5)
+    g = torch.Generator(device="cuda").manual_seed(22)
+    ub = torch.view_as_complex(torch.randn((batch, n, 2), generator=g, device="cuda"))
+    got = plan.forward(ub)
+    for b in (0, 1, 1001, batch - 2, batch - 1):
+        u = ub[b].contiguous()
+        assert rel_l2(got[b].cpu().numpy(), _oracle(x, d, u.cpu().numpy(), lam, z0, 8e-6, m)) <= TOL
+        assert rel_l2(got[b].cpu().numpy(), plan.forward(u).cpu().numpy()) <= TOL
+    plan.close()
