@@ -42,7 +42,7 @@ PROFILE_TRAFFIC = os.path.join(ROOT, "profiles", "spread_cap_2048_traffic.txt")
 PROFILE_FFT = os.path.join(ROOT, "profiles", "fft_counters_cap_2048.txt")
 CSRC = os.path.join(ROOT, "paper_1203_3583_amd", "csrc")
 SPREAD_SOURCE = os.path.join(CSRC, "spread.hip")
-FFT_SOURCE = os.path.join(CSRC, "fft.hip")
+FFT_SOURCES = [os.path.join(CSRC, f) for f in ("fft.hip", "fft_engine.h")]
 GOLDEN = os.path.join(ROOT, "tests", "golden", "make_eval_sets.py")
 
 
@@ -87,11 +87,11 @@ def _summary_fields(path):
     return fields
 
 
-def _code_sha(path):
-    """SHA-256 of a C++/HIP source's code: comments removed and whitespace collapsed,
+def _code_sha(*paths):
+    """SHA-256 of C++/HIP sources' code: comments removed and whitespace collapsed,
     so that a stored counter summary stays tied to the code it was measured on and
     not to the wording of its comments."""
-    text = open(path, encoding="utf-8").read()
+    text = "\n".join(open(path, encoding="utf-8").read() for path in paths)
     text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
     text = re.sub(r"//[^\n]*", " ", text)
     return hashlib.sha256(" ".join(text.split()).encode()).hexdigest()
@@ -115,7 +115,7 @@ def stored_fft_busy():
     cores, SQ_VALU_MFMA_BUSY_CYCLES; each over GRBM_GUI_ACTIVE and the SIMD count),
     if it was taken on the current FFT code (else None)."""
     fields = _summary_fields(PROFILE_FFT)
-    if fields.get("fft_code_sha256") != _code_sha(FFT_SOURCE):
+    if fields.get("fft_code_sha256") != _code_sha(*FFT_SOURCES):
         return None
     out = {}
     for k, v in fields.items():

@@ -32,3 +32,29 @@ def test_workloads_name_the_configs():
     for name in bench.WORKLOADS:
         w = synth.config(name, side=16)
         assert w.name == name
+
+
+def test_stored_fft_counters_are_of_the_current_engine(tmp_path, monkeypatch):
+    """Counters taken on other code of the FFT passes, the kernels' or the engine's, are not
+    reported; another wording of the comments does not matter."""
+    sys.path.insert(0, ROOT)
+    import bench
+
+    names = [os.path.basename(p) for p in bench.FFT_SOURCES]
+    assert sorted(names) == ["fft.hip", "fft_engine.h"]
+    copies = []
+    for p in bench.FFT_SOURCES:
+        copies.append(tmp_path / os.path.basename(p))
+        copies[-1].write_text(open(p, encoding="utf-8").read(), encoding="utf-8")
+    monkeypatch.setattr(bench, "FFT_SOURCES", [str(p) for p in copies])
+    summary = tmp_path / "summary.txt"
+    summary.write_text(f"busy_pass1_fp32_valu: 0.5\nfft_code_sha256: {bench._code_sha(*bench.FFT_SOURCES)}\n")
+    monkeypatch.setattr(bench, "PROFILE_FFT", str(summary))
+    assert bench.stored_fft_busy() == {"pass1_fp32_valu": 0.5}
+    for p in copies:
+        text = p.read_text(encoding="utf-8")
+        p.write_text("// a comment\n" + text, encoding="utf-8")
+        assert bench.stored_fft_busy() == {"pass1_fp32_valu": 0.5}
+        p.write_text(text + "\nint other;\n", encoding="utf-8")
+        assert bench.stored_fft_busy() is None
+        p.write_text(text, encoding="utf-8")
