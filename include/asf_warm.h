@@ -78,7 +78,8 @@ int asf_warm_conv3x3_masked(const float *in, const uint16_t *w, const float *act
                             int32_t W, int32_t cin, int32_t cout, void *stream);
 
 /* asf_warm_conv3x3_wgrad of the decoder's concatenated input, read in place as
- * asf_warm_conv3x3_upcat reads it (any size; c_low, c_skip and cout multiples of 32). */
+ * asf_warm_conv3x3_upcat reads it: H, W even, B H W below 2^22, c_low, c_skip and cout
+ * multiples of 32 (-1 otherwise; layers of any number of tiles). */
 int asf_warm_conv3x3_wgrad_upcat(const float *low, int32_t c_low, const float *skip, int32_t c_skip,
                                  const float *dout, float *dw, float *dbias, int32_t B, int32_t H, int32_t W,
                                  int32_t cout, void *stream);

@@ -132,8 +132,8 @@ def _fused_loss_takes(plan, theta, amp, target):
     """Whether the fused loss computes this call: plain contiguous tensors of the plan's
     sizes on its device, nothing but theta differentiated.  Everything else (broadcast or
     strided arguments, other types, gradients of amp or target) takes the composite of
-    elementwise operations.  On every call the fused form takes it is the faster one, four
-    launches and 0.13 GB beside the transforms against about thirty and 1.0 GB at 1024^2
+    elementwise operations.  On every call the fused form takes it is the faster one, five
+    launches and 0.09 GB beside the transforms against about thirty and 1.0 GB at 1024^2
     points (there one gradient takes 154 us, against 346)."""
     torch = _torch()
     # tracing and forward-mode levels see the elementwise operations

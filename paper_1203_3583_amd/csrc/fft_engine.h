@@ -170,8 +170,10 @@ struct Dft16Split16 {
         accr = __builtin_amdgcn_mfma_f32_16x16x32_f16(re_hi, bh, accr, 0, 0, 0);
         acci = __builtin_amdgcn_mfma_f32_16x16x32_f16(im_hi, bh, acci, 0, 0, 0);
         // the products are read here, in the block that issued them: where the first read
-        // of the accumulators was left behind a branch (a store under a flag), the compiler
-        // put no wait states on the taken path and the read returned stale values
+        // of the accumulators is left behind a branch (the flag of the adjoint rows' stores),
+        // the compiler puts no wait states on the taken path and the read returned stale
+        // values (without this, rows of 32, 64, 256, 512 and 1024 points read the sums two to
+        // four instructions after the last product, past an s_cbranch)
         asm volatile("" : "+v"(accr), "+v"(acci));
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = make_float2(accr[i], acci[i]);

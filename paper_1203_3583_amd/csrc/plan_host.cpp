@@ -154,8 +154,10 @@ int make_line_layout(int64_t n, const asf_line_params *p, LineLayout &L) {
     };
     L.off_status = take(kAlign);
     // per point w coefficients (4 bytes), the phase factor and the index, per cell its run's
-    // first point and first coefficient, packed: less than 8 + 8 w bytes per point unless
-    // the points are few for the line
+    // first point and first coefficient, packed: 12 + 4 w bytes per point.  The region is
+    // never below 8 + 8 w bytes per point, the size of complex coefficients with their index
+    // and cell: plans were that large when the coefficients were complex, the check of the
+    // layouts still asks for 8 w, and the most it leaves unused is 0.5 MB (16384 points, w = 9)
     const size_t region = o;
     L.off_coef = o;
     L.off_phase = L.off_coef + (4 * (size_t)L.n * L.w + 7) / 8 * 8;

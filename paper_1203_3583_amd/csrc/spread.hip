@@ -393,13 +393,16 @@ __device__ inline int split_emax(uint32_t nrec) {
 // What a workgroup knows of its tile (uniform), and its LDS.  Its three ways through a
 // tile -- small (one batch of records, kept in registers), large (several batches) and
 // cut_slice -- are separate code with packed and split sums separate again: in one body
-// their registers add up past the 80 that six waves per SIMD leave, and a batch fetched
-// ahead is spilled, which waits for it.  Bound by latency (the chain of dependent loads
-// per tile: slots, keys, field) and by the 49 LDS atomics per record, which the next
-// batch's loads overlap: 2048^2 cap (8192 small tiles) 126.5 -> 114.8 us, 4096^2 relief
-// (large) 501 -> 474, 1024^2 at w = 9 with split sums 84.3 -> 48.3; since the tiles are
-// taken in order of size (the binning's tile_order) 105, 342 and 40 us.  The cap's
-// records, field and cells are 300 MB, 59 us at the rate of a large copy.
+// with the next batch fetched ahead 29 to 49 of the 80 registers that six waves per SIMD
+// leave were spilled, the batch in flight among them, which waits for it.  Apart, 20 are
+// at w = 7 (8 to 16 below, 37 and 60 at w = 8 and 9), some of them reloaded in the batch
+// loops; without a batch fetched ahead none were, and the kernel was slower all the same.
+// Bound by latency (the chain of dependent loads per tile: slots, keys, field) and by the
+// 49 LDS atomics per record, which the next batch's loads overlap: 2048^2 cap (8192 small
+// tiles) 126.5 -> 114.8 us, 4096^2 relief (large) 501 -> 474, 1024^2 at w = 9 with split
+// sums 84.3 -> 48.3; since the tiles are taken in order of size (the binning's tile_order)
+// 105, 342 and 40 us.  The cap's records, field and cells are 300 MB, 59 us at the rate of
+// a large copy.
 template <int W>
 struct Tile {
     using G = TileGeom<W>;

@@ -240,8 +240,9 @@ __global__ __launch_bounds__(256) void conv3x3_tiled_kernel(
 // two workgroups, else 4 or 2 rows, so that the deep, small layers still spread
 // over the whole chip (128^2, 384 -> 128 channels: 28.6 us with 4-row tiles, 36.9 with
 // 2-row tiles, which fetch the weights twice as often; 64^2, 128 -> 256: 9.4 with 2 rows,
-// 10.6 with 4).  8-row tiles take 512 threads, so that a thread's share of a slice still
-// fits its registers.
+// 10.6 with 4).  8-row tiles take 512 threads: with 256 a thread's share of a slice no
+// longer fits the 128 registers of four waves per SIMD (21 -> 31 us).  4-row tiles have 256,
+// and 15 registers spilled where the input is a concatenation (1 where it is not).
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 constexpr int64_t kConvWorkgroupsWanted = 512;   // two per CU
 
@@ -393,15 +394,17 @@ __global__ __launch_bounds__(NT, 4) void conv3x3_tiled32_kernel(
 // with FP32 atomics, one set per workgroup: eight waves share it, where four waves and
 // twice the workgroups took 45 us for 512^2 pixels, 32 -> 32 channels (now 31; 13 us are
 // the bytes of a large copy) and 76 us for 128^2, 384 -> 128 (now 51).  Bound by latency
-// (one or two workgroups per CU, each waiting at two barriers per tile) and by the atomics
-// (another 256 sets of them cost 9 us).
+// (one or two workgroups per CU, each waiting at two barriers per tile; of the 128 registers
+// of four waves per SIMD 10 are spilled and reloaded in the tile loop, 20 where the input is
+// a concatenation) and by the atomics (another 256 sets of them cost 9 us).
 constexpr int kWgTH = 8;                                // tile rows: the contraction's 32-pixel steps
 constexpr int kWgDPitch = kWgTH * 32 + 8;               // dout tile, per output channel (elements)
 constexpr int kWgXCols = 48;                            // input halo columns x0 - 8 .. x0 + 39
 constexpr int kWgXPitch = (kWgTH + 2) * kWgXCols + 8;   // input halo, per input channel (elements)
 constexpr int kWgThreads = 512;
 
-constexpr int kMaxWgradPix = 1 << 22;   // B H W below this
+// B H W below this: the refusal the header states (the kernel's own indices reach further)
+constexpr int kMaxWgradPix = 1 << 22;
 
 template <bool CAT>
 __global__ __launch_bounds__(kWgThreads, 4) void conv3x3_wgrad_kernel(
