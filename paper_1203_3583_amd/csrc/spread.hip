@@ -396,7 +396,7 @@ __device__ inline int split_emax(uint32_t nrec) {
 // with the next batch fetched ahead 29 to 49 of the 80 registers that six waves per SIMD
 // leave were spilled, the batch in flight among them, which waits for it.  Apart, 20 are
 // at w = 7 (8 to 16 below, 37 and 60 at w = 8 and 9), some of them reloaded in the batch
-// loops; without a batch fetched ahead none were, and the kernel was slower all the same.
+// loops; without a batch fetched ahead none were from w = 3 on, and the kernel was slower.
 // Bound by latency (the chain of dependent loads per tile: slots, keys, field) and by the
 // 49 LDS atomics per record, which the next batch's loads overlap: 2048^2 cap (8192 small
 // tiles) 126.5 -> 114.8 us, 4096^2 relief (large) 501 -> 474, 1024^2 at w = 9 with split
