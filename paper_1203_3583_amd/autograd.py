@@ -64,11 +64,13 @@ class _IntensityLoss:
             from . import asf as _asf
 
             class IntensityLoss(torch.autograd.Function):
-                # The field u1 is an output beside the loss: saved as one, it links a graph of
-                # the gradient to theta as it was at the forward, and nothing of the caller's
-                # (theta, amp, target may change in place) is read again.
+                # A graph of the gradient (create_graph) is that of the values the loss was computed
+                # from: nothing of the caller's (theta, amp, target may change in place) is read
+                # again, and theta only links the graph.  A leaf has no history to change and links
+                # it as it is; for any other theta (link) the field u1 is an output beside the loss
+                # and, saved as one, links it through this node.  (An output more costs 5 us.)
                 @staticmethod
-                def forward(ctx, theta, plan, amp, target):
+                def forward(ctx, theta, plan, amp, target, link):
                     L = _asf.lib()
                     dev, m = plan.device, plan.mx * plan.my
                     s = _asf._stream_ptr(torch, dev, None)
@@ -83,19 +85,25 @@ class _IntensityLoss:
                     _asf._check(L.asf_intensity_loss(m, u2.data_ptr(), target.data_ptr(),
                                                      int(target.dtype == torch.float64), diff, diff + 8 * m,
                                                      loss.data_ptr(), s))
-                    ctx.set_materialize_grads(False)
                     ctx.save_for_backward(u1, u2, buf)
-                    ctx.plan, ctx.theta = plan, (theta.shape, theta.dtype)
+                    ctx.plan, ctx.shape, ctx.dtype = plan, theta.shape, theta.dtype
+                    if not link:
+                        ctx.leaf = theta
+                        return loss
+                    ctx.leaf = None
+                    ctx.set_materialize_grads(False)
                     return loss, u1
 
                 @staticmethod
-                def backward(ctx, grad, g1):
+                def backward(ctx, grad, g1=None):
                     """grad: of the loss, g1: of u1 (from a graph of the gradient); None: none."""
                     plan = ctx.plan
                     u1, u2, buf = ctx.saved_tensors
                     m = plan.mx * plan.my
-                    shape, dtype = ctx.theta
                     if torch.is_grad_enabled():   # create_graph: the same in differentiable operations
+                        if ctx.leaf is not None:   # u1 exp(i (theta - theta))
+                            turn = (ctx.leaf - ctx.leaf.detach()).to(torch.float32).reshape(-1)
+                            u1 = (u1 * torch.polar(torch.ones_like(turn), turn)).requires_grad_()
                         if grad is not None:
                             u = _Propagate.get().apply(u1, plan, u2)
                             inten = u.real.double() ** 2 + u.imag.double() ** 2
@@ -103,8 +111,10 @@ class _IntensityLoss:
                             d = buf[:m].view(plan.my, plan.mx) + (inten - inten.detach())
                             part = torch.autograd.grad((d ** 2).sum() / buf[m], u1, grad, create_graph=True)[0]
                             g1 = part if g1 is None else g1 + part
-                        out = None if g1 is None else (g1.conj() * (1j * u1)).real.to(dtype).reshape(shape)
-                        return out, None, None, None
+                        out = None if g1 is None else (g1.conj() * (1j * u1)).real.to(ctx.dtype).reshape(ctx.shape)
+                        return out, None, None, None, None
+                    if grad is None and g1 is None:
+                        return None, None, None, None, None
                     L = _asf.lib()
                     dev = plan.device
                     s = _asf._stream_ptr(torch, dev, None)
@@ -116,13 +126,12 @@ class _IntensityLoss:
                                                                   grad.data_ptr(), g2.data_ptr(), s))
                         part = plan.adjoint(g2)
                         g1 = part if g1 is None else g1 + part
-                    if g1 is None:
-                        return None, None, None, None
-                    g1 = g1.resolve_conj().contiguous()
-                    out = torch.empty(shape, dtype=dtype, device=dev)
+                    else:
+                        g1 = g1.resolve_conj().contiguous()
+                    out = torch.empty(ctx.shape, dtype=ctx.dtype, device=dev)
                     _asf._check(L.asf_phase_backward(plan.n, u1.data_ptr(), g1.data_ptr(), out.data_ptr(),
-                                                     int(dtype == torch.float64), s))
-                    return out, None, None, None
+                                                     int(ctx.dtype == torch.float64), s))
+                    return out, None, None, None, None
 
             cls.fn = IntensityLoss
         return cls.fn
@@ -166,7 +175,9 @@ def intensity_loss(plan, theta, amp, target):
     target: real [my, mx] tensor in the units of |u2|^2 (see ``energy_matched``).
     """
     if _fused_loss_takes(plan, theta, amp, target):
-        return _IntensityLoss.get().apply(theta, plan, amp, target)[0]
+        link = theta.grad_fn is not None
+        out = _IntensityLoss.get().apply(theta, plan, amp, target, link)
+        return out[0] if link else out
     return _intensity_loss_composite(plan, theta, amp, target)
 
 
