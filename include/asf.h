@@ -164,7 +164,11 @@ int asf_plan(asf_plan_t *out, int64_t n_src, const double *x1, const double *y1,
  * Calls on one plan are ordered by the caller's stream: a later forward, adjoint
  * or asf_status sees this binning, and the binning after it reuses the counters
  * of the one before (binnings alternate between two copies), so do not issue a
- * setpts on another stream while work of the same plan is in flight.
+ * setpts on another stream while work of the same plan is in flight.  From the
+ * first call on the plan that is captured into a graph, binnings stay with one copy
+ * and clear it first: graphs holding asf_setpts, asf_forward or asf_adjoint may be
+ * replayed any number of times, among calls outside them, each seeing the binning
+ * before it.
  * Returns ASF_OK, ASF_EINVAL or ASF_EHIP.
  */
 int asf_setpts(asf_plan_t plan, const double *x1, const double *y1, const double *d1,

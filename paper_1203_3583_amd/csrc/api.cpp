@@ -67,6 +67,7 @@ struct asf_plan_s {
     bool sparse;        // many tiles empty last time: leave them unwritten, the column pass reads zeros
     int copy;           // which copy of status and cursor the last binning used
     bool clear_both;    // clear both copies first (new plan, or a failed binning launch)
+    bool captured;      // launches of this plan were captured into a graph: the copy they name stays in use
     uint32_t slots;     // workgroups resident at once (crowded tiles are cut against it); 0: never cut
     bool events;
     hipEvent_t ev[2 * asf::NSTAGES];
@@ -103,6 +104,20 @@ struct StageMark {
     }
 };
 
+// A graph's launches keep naming the copy of the counters that was in use when they were
+// captured, and may be replayed any number of times: from the first capture on, the plan's
+// binnings stay with that copy and clear it first, by a launch of their own (4 us), instead of
+// relying on the binning before to have cleared the other one.
+void note_capture(asf_plan_s *p, hipStream_t s) {
+    if (p->captured) return;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();   // the default stream while another one captures
+        return;
+    }
+    p->captured = st == hipStreamCaptureStatusActive;
+}
+
 // Point bin.status and bin.cursor at copy p->copy of the counters, and the
 // next_ pointers at the other copy.
 void bind_counters(asf_plan_s *p) {
@@ -118,7 +133,7 @@ int geometry_launches(asf_plan_s *p, const double *x, const double *y, const dou
     hipError_t e;
     {
         StageMark m(p, asf::STAGE_BIN, s);
-        if (p->clear_both) {
+        if (p->clear_both || p->captured) {
             e = asf::launch_bin_reset(p->bin, p->lay.ntiles, s);
             if (e != hipSuccess) return hip_fail(e, "bin_reset launch");
         }
@@ -146,7 +161,8 @@ int geometry_launches(asf_plan_s *p, const double *x, const double *y, const dou
 
 // One binning, into the counters the previous binning's second pass cleared.
 int run_geometry(asf_plan_s *p, const double *x, const double *y, const double *d, hipStream_t s) {
-    p->copy ^= 1;
+    note_capture(p, s);
+    if (!p->captured) p->copy ^= 1;
     bind_counters(p);
     const int rc = geometry_launches(p, x, y, d, s);
     p->clear_both = rc != ASF_OK;
@@ -261,6 +277,7 @@ int asf_plan(asf_plan_t *out, int64_t n_src, const double *x1, const double *y1,
     char *w = pl->ws;
     pl->copy = 1;   // the first binning takes copy 0
     pl->clear_both = true;
+    pl->captured = false;
     bind_counters(pl);
     pl->bin.tile_start = reinterpret_cast<uint32_t *>(w + L.off_tile_start);
     pl->bin.key = reinterpret_cast<uint2 *>(w + L.off_cell);
@@ -379,6 +396,7 @@ int forward_into(asf_plan_t plan, const void *u1, void *u2, void *stream, int ac
                  float2 *mid) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     asf_plan_s *p = plan;
+    note_capture(p, s);
     const int split = (p->prm.flags & ASF_FFT_MASK) == ASF_FFT_SPLIT_FP16;
     hipError_t e;
     {
@@ -438,6 +456,7 @@ int asf_adjoint(asf_plan_t plan, const void *g2, void *g1, void *stream) {
     if (!plan || !g2 || !g1) return fail(ASF_EINVAL, "plan, g2, g1 must be non-NULL");
     hipStream_t s = static_cast<hipStream_t>(stream);
     asf_plan_s *p = plan;
+    note_capture(p, s);
     const int split = (p->prm.flags & ASF_FFT_MASK) == ASF_FFT_SPLIT_FP16;
     hipError_t e;
     {
